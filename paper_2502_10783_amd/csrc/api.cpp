@@ -476,13 +476,16 @@ ipp_status run_cached(IppCtx* c, std::vector<uint8_t> key, const Plan& P,
 // ---- kernel sequences --------------------------------------------------
 ipp_status run_mesh(IppCtx* c, const Plan& P, const Work& w,
                     const ipp_params& p, bool clear, hipStream_t s) {
-  const int area = p.mesh_h * p.mesh_w;
+  // a region is loaded in groups of four columns of a row, PPL / 4 of them a
+  // lane: the kernels take what their lanes hold, rows that are not whole
+  // groups rounded up
+  const int groups = p.mesh_h * ((p.mesh_w + 3) / 4);
   const dim3 gw((P.nodes + kRowWaves - 1) / kRowWaves);
-  if (area <= 16 * kWave)
+  if (groups <= 16 / 4 * kWave)
     IPP_LAUNCH(c, s, "k_mesh_stats",
                hipLaunchKernelGGL(k_mesh_stats_w<16>, gw, dim3(kRowThreads), 0,
                                   s, w, p));
-  else if (area <= 64 * kWave)
+  else if (groups <= 64 / 4 * kWave)
     IPP_LAUNCH(c, s, "k_mesh_stats",
                hipLaunchKernelGGL(k_mesh_stats_w<64>, gw, dim3(kRowThreads), 0,
                                   s, w, p));

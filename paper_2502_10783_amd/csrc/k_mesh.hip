@@ -455,8 +455,9 @@ __global__ __launch_bounds__(kBlock) void k_mesh_stats(Work wk,
 }
 
 // ---------------------------------------------------------------------
-// k_mesh_stats_w: one wavefront per region for regions of at most 64 * PPL
-// pixels (no workgroup barriers).  Same selection scheme as k_mesh_stats,
+// k_mesh_stats_w: one wavefront per region for regions of at most 64 * PPL / 4
+// groups of four columns, a row's last group counted whole (no workgroup
+// barriers).  Same selection scheme as k_mesh_stats,
 // with wave-level histograms of 16-bit counts (two per LDS word), ballot
 // counts, and one fused pass per clipping step that counts the new set and
 // sums its moments about a fixed shift c0 (the sample median).
