@@ -144,19 +144,18 @@ class SourceTable:
     def __init__(self, capacity: int, n_frames: int, device):
         self.capacity = int(capacity)
         self.n_frames = n_frames
-        # the columns of one type are the rows of one zeroed buffer (256-byte
-        # aligned): three fills instead of one per column
+        # every column a tensor of its own (a program may differentiate, save
+        # or resize one without the others), those of one type cleared in one
+        # launch
         n = max(1, int(capacity))
-        self.cols = {name: None for name, _ in L.SOURCE_COLUMNS}
-        for dt in (torch.int32, torch.float64):
-            names = [name for name, d in L.SOURCE_COLUMNS
-                     if self.DT[d] == dt]
-            buf = torch.zeros((len(names), -(-n // 64) * 64), dtype=dt,
-                              device=device)
-            self.cols.update(zip(names, buf[:, :n].unbind(0)))
-        counts = torch.zeros(32 + n_frames + 1, dtype=torch.int64,
-                             device=device)
-        self.n_total, self.frame_offsets = counts[:1], counts[32:]
+        self.cols = {name: torch.empty(n, dtype=self.DT[d], device=device)
+                     for name, d in L.SOURCE_COLUMNS}
+        self.n_total = torch.empty(1, dtype=torch.int64, device=device)
+        self.frame_offsets = torch.empty(n_frames + 1, dtype=torch.int64,
+                                         device=device)
+        new = [self.n_total, self.frame_offsets, *self.cols.values()]
+        for dt in (torch.int32, torch.int64, torch.float64):
+            torch._foreach_zero_([t for t in new if t.dtype == dt])
 
     def to_c(self, n_total=True) -> L.IppSources:
         s = L.IppSources()
