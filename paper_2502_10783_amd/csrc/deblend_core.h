@@ -53,7 +53,7 @@ struct Chain {
   double F_top;              // intensity above its level of the top node
   int64_t nobj_sum;          // objects of the significant child chains
   int32_t parent;            // chain of the parent node (-1: the root)
-  int32_t last, top;         // levels of the chain's highest and top node
+  int16_t last, top;         // levels of the chain's highest and top node
   int32_t nsig;              // significant child chains
   int32_t one;               // a significant child chain (nsig == 1)
   int32_t nobj;              // objects this chain stands for
@@ -65,6 +65,9 @@ struct Chain {
   int32_t slot;              // seed index of an object chain
   int32_t first;             // first pixel of an object chain's seed
 };
+
+// the scratch of a candidate that ipp.h states
+static_assert(sizeof(Chain) == 64 && kMaxLevels <= 0x7FFF, "a chain record");
 
 // One seed / object.  m[s][j]: limb j of the seed sums S = sum d,
 // Sx = sum d dx, Sy = sum d dy, Sxx = sum d dx^2, Syy = sum d dy^2 (dx, dy
@@ -78,6 +81,7 @@ struct Obj {
   int32_t xmin, ymin, first, target;
   int32_t final_obj, idx;    // object after merges; survivor number
 };
+static_assert(sizeof(Obj) == 240, "an object record");
 
 __host__ __device__ inline size_t align16(size_t b) { return (b + 15) & ~(size_t)15; }
 
@@ -181,7 +185,7 @@ __host__ __device__ inline int high_bit(uint64_t v) {
 // What the tree knows of a chain when it starts (F_top, parent and top
 // follow when it ends), and the fields that the pruning fills.
 __host__ __device__ inline void chain_start(Chain& c, int level, bool sig) {
-  c.last = level;
+  c.last = (int16_t)level;
   c.allsig = sig ? 1 : 0;
 }
 __host__ __device__ inline void chain_clear(Chain& c) {
@@ -348,7 +352,7 @@ __host__ __device__ inline int build_tree(const G& g, M& m, int conn, int bw,
         const int r = comp_root(j, o), c = comp_chain(j);
         if (m.num(r) & kTwo) {
           chains[c].F_top = intensity(o, lv + 1);
-          chains[c].top = lv + 1;
+          chains[c].top = (int16_t)(lv + 1);
           fresh = r == o;
         } else {
           m.set_chn(r, c);
