@@ -734,7 +734,7 @@ DeblendWs deblend_layout(size_t base, int32_t n, int64_t cap) {
   D.o_cnt = take(8 * rows);
   D.o_ooff = take(8 * rows);
   D.o_blk = take(8 * (size_t)(D.nblk + 1));
-  D.o_tot = take(8 * (8 + kDbQueues * kDbQueueStep));
+  D.o_tot = take(8 * 8);
   D.o_big = take(4 * rows);
   D.o_pool = o;
   return D;
@@ -1568,18 +1568,19 @@ ipp_status ipp_deblend(void* ctx, const ipp_frame* frames, int32_t n,
   IPP_LAUNCH(c, s, "k_fill_i64",
              hipLaunchKernelGGL(k_fill_i64, dim3(1), dim3(64), 0, s,
                                 w.counters, (int64_t)4, (int64_t)0));
-  // tot[3], tot[6], tot[8] ..: the three kernels' queue counters; tot[4],
-  // tot[5]: the lengths of the workgroup kernels' lists (k_db_large's from
-  // the front of `big`, k_db_mid's from its back)
+  // tot[3], tot[6], tot[7]: the three kernels' queue counters (k_db_small's
+  // lie in ooff if they are several); tot[4], tot[5]: the lengths of the
+  // workgroup kernels' lists (k_db_large's from the front of `big`,
+  // k_db_mid's from its back)
+  int64_t* queue = db_queues(cap) > 1 ? ooff : tot + 7;
   IPP_LAUNCH(c, s, "k_fill_i64",
              hipLaunchKernelGGL(k_fill_i64, dim3(1), dim3(64), 0, s, tot + 2,
-                                (int64_t)6 + kDbQueues * kDbQueueStep,
-                                (int64_t)0));
+                                (int64_t)6, (int64_t)0));
   IPP_LAUNCH(c, s, "k_db_need",
              hipLaunchKernelGGL(k_db_need,
                                 dim3(grid_for(rows, kBlock, 16384)),
                                 dim3(kBlock), 0, s, *cand, need, big,
-                                tot + 4));
+                                tot + 4, queue));
   if ((st = scan64(c, need, blk, D.nblk, off, rows, tot, s)) != IPP_OK)
     return st;
   // persistent workgroups (as many as fit the device at once) that take
@@ -1601,7 +1602,7 @@ ipp_status ipp_deblend(void* ctx, const ipp_frame* frames, int32_t n,
     Fork fork(c, s);
     IPP_DB(k_db_large, kDbLargePerCu, 8 * kWave, tot + 3, fork.side);
     IPP_DB(k_db_mid, kDbMidPerCu, 4 * kWave, tot + 6, s);
-    IPP_DB(k_db_small, kDbSmallPerCu, kWave, tot + 8, s);
+    IPP_DB(k_db_small, kDbSmallPerCu, kWave, queue, s);
   }
 #undef IPP_DB
   if ((st = scan64(c, cnt, blk, D.nblk, ooff, rows, tot + 1, s)) != IPP_OK)

@@ -61,9 +61,11 @@ __device__ __forceinline__ int db_class(int64_t A, double peak, int m) {
 __global__ __launch_bounds__(kBlock) void k_db_need(ipp_sources cand,
                                                     int64_t* need,
                                                     int32_t* big,
-                                                    int64_t* nbig) {
+                                                    int64_t* nbig,
+                                                    int64_t* queue) {
   const long long n = table_rows(cand);
   const long long rows = cand.capacity + 1;
+  const int nq = db_queues(cand.capacity);
   for (long long r = blockIdx.x * (long long)kBlock + threadIdx.x;
        r <= cand.capacity; r += (long long)gridDim.x * kBlock) {
     int64_t u = 0;
@@ -85,6 +87,7 @@ __global__ __launch_bounds__(kBlock) void k_db_need(ipp_sources cand,
       }
     }
     need[r] = u;
+    if (nq > 1 && r < nq * kDbQueueStep) queue[r] = 0;
   }
 }
 
@@ -1108,9 +1111,10 @@ __device__ __forceinline__ void db_groups(
   }
   if (!fits) return;
   const long long nlist = CLS == 0 ? n : (CLS == 2 ? nbig[0] : nbig[1]);
-  // class 0 takes its rows from kDbQueues counters, a workgroup from one of
+  // class 0 takes its rows from several counters, a workgroup from one of
   // them (thousands of short candidates queue up at one address: 12 ns each)
-  const int qi = CLS == 0 ? blockIdx.x % kDbQueues : 0;
+  const int nq = CLS == 0 ? db_queues(cand.capacity) : 1;
+  const int qi = CLS == 0 ? blockIdx.x % nq : 0;
   while (true) {
     if (g.tid == 0)
       next_row = (long long)atomicAdd(
@@ -1118,7 +1122,7 @@ __device__ __forceinline__ void db_groups(
     __syncthreads();
     long long r = next_row;
     __syncthreads();
-    if (CLS == 0) r = r * kDbQueues + qi;
+    if (CLS == 0) r = r * nq + qi;
     if (r >= nlist) break;
     if (CLS == 2) r = big[r];
     if (CLS == 1) r = big[cand.capacity - r];

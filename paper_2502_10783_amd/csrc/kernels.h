@@ -101,9 +101,10 @@ hipError_t asinh_scratch(int device, double** ptr);
 // Deblending (k_deblend.hip): see that file for the sequence.
 // need: scratch units per row; big / nbig: the rows of the workgroup
 // kernels, k_db_large's from the front (nbig[0]), k_db_mid's from the back
-// (nbig[1]); nbig zeroed by the caller.
+// (nbig[1]); nbig zeroed by the caller.  queue: k_db_small's counters,
+// cleared if they are several (the caller clears a single one).
 __global__ void k_db_need(ipp_sources cand, int64_t* need, int32_t* big,
-                          int64_t* nbig);
+                          int64_t* nbig, int64_t* queue);
 __global__ void k_scan64_blocks(const int64_t* in, int64_t* blocks,
                                 int64_t n);
 __global__ void k_scan64_top(int64_t* blocks, int64_t nblocks,
@@ -114,9 +115,14 @@ __global__ void k_scan64_apply(const int64_t* in, const int64_t* blocks,
 // a workgroup of four, larger ones one of eight, in LDS up to kDbBigBox.
 constexpr int kDbSmallBox = 512, kDbMidBox = 2048, kDbBigBox = 6144;
 // Resident workgroups per compute unit of the three kernels (by their LDS);
-// queue: a zeroed counter of taken rows (k_db_small: kDbQueues of them,
-// kDbQueueStep words apart).
+// queue: a zeroed counter of taken rows (k_db_small: db_queues(capacity) of
+// them, kDbQueueStep words apart).  The several counters lie where the object
+// offsets go once the candidates are done, if those take so many words; short
+// tables have one counter.
 constexpr int kDbQueues = 16, kDbQueueStep = 16;
+__host__ __device__ inline int db_queues(int64_t capacity) {
+  return capacity + 1 >= kDbQueues * kDbQueueStep ? kDbQueues : 1;
+}
 constexpr int kDbSmallPerCu = 11, kDbMidPerCu = 3, kDbLargePerCu = 1;
 #define IPP_DB_DECLARE(NAME)                                                  \
   __global__ void NAME(Work wk, ipp_sources cand, const int64_t* off,         \
