@@ -1695,7 +1695,7 @@ ipp_status ipp_photometry_auto(void* ctx, const ipp_frame* frames, int32_t n,
     return fail(c, IPP_E_DEVICE, std::string("descriptor upload failed: ") +
                                      hipGetErrorString(e));
   // the part tables share what the workspace has left (a part without an
-  // entry is still summed, by the finishing workgroup)
+  // entry is still summed, by a workgroup that takes the row)
   const size_t o = align_up(P.total);
   const size_t rest = c->ws_bytes > o ? c->ws_bytes - o : 0;
   const int64_t cap = (int64_t)std::min<size_t>(
@@ -1703,10 +1703,9 @@ ipp_status ipp_photometry_auto(void* ctx, const ipp_frame* frames, int32_t n,
   KronPart* parts = (KronPart*)((char*)c->ws + o);
   const KronTable t1 = {w.counters, parts, cap};
   const KronTable t2 = {w.counters + 1, parts + cap, cap};
-  const dim3 b(kBlock), bb(kBigThreads);
-  const dim3 gp((unsigned)std::max(1, std::min<int>((int)(cap / kWaves),
-                                                    8 * c->n_cu)));
-  const dim3 gf(grid_for(src->capacity, kBigThreads, 4 * c->n_cu));
+  const dim3 b(kBlock);
+  const dim3 gp(std::max(grid_for(cap, kWaves, 8 * c->n_cu),
+                         grid_for(src->capacity, kWave, 4 * c->n_cu)));
   IPP_LAUNCH(c, s, "k_kron",
              hipLaunchKernelGGL(k_kron,
                                 dim3(grid_for(src->capacity, kRowWaves,
@@ -1717,18 +1716,12 @@ ipp_status ipp_photometry_auto(void* ctx, const ipp_frame* frames, int32_t n,
                                 area, flags));
   IPP_LAUNCH(c, s, "k_kron_parts",
              hipLaunchKernelGGL((k_kron_parts<1>), gp, b, 0, s, w, *src, mom,
-                                a.search, t1, kron));
-  IPP_LAUNCH(c, s, "k_kron_finish",
-             hipLaunchKernelGGL((k_kron_finish<1>), gf, bb, 0, s, w, *src,
-                                mom, a.kron_factor, a.kron_min, a.search, t1,
-                                t2, kron, flux, area, flags));
+                                a.kron_factor, a.kron_min, a.search, t1, t2,
+                                kron, flux, area, flags));
   IPP_LAUNCH(c, s, "k_kron_parts",
              hipLaunchKernelGGL((k_kron_parts<2>), gp, b, 0, s, w, *src, mom,
-                                a.search, t2, kron));
-  IPP_LAUNCH(c, s, "k_kron_finish",
-             hipLaunchKernelGGL((k_kron_finish<2>), gf, bb, 0, s, w, *src,
-                                mom, a.kron_factor, a.kron_min, a.search, t2,
-                                t2, kron, flux, area, flags));
+                                a.kron_factor, a.kron_min, a.search, t2, t2,
+                                kron, flux, area, flags));
   return IPP_OK;
 }
 

@@ -448,18 +448,31 @@ __device__ void kron_pass2(const FrameDev& fr, const KronRow& r,
 
 // Parts of the windows left to the whole grid: per pass a count of parts,
 // and per part its row, its number within the row and its sums (KronPart).
-// A row's parts are consecutive; the first one's index is kept in area[row]
-// until the row is finished (-1: the table was full, the finishing workgroup
-// sums the parts itself).
+// A row's parts are consecutive; the first one's `done` counts the parts that
+// are summed (and notes a member off the frame).  A row that finds the table
+// full carries a bit in its flags until it is finished.
 namespace {
+constexpr int kPartEdge = 1 << 30;                   // in done
+constexpr uint32_t kKronLeft1 = 1u << 31, kKronLeft2 = 1u << 30;
+
 __device__ __forceinline__ int kron_parts(int npx) {
   return (npx + kKronPart - 1) / kKronPart;
 }
 
+// A part's sum stored and loaded where every XCD sees it.
+__device__ __forceinline__ void part_store(double* p, double v) {
+  __hip_atomic_store((long long*)p, __double_as_longlong(v), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double part_load(const double* p) {
+  return __longlong_as_double(__hip_atomic_load(
+      (const long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
 // Reserves and fills the part entries of a row; wave-uniform result.
-__device__ __forceinline__ long long kron_reserve(const KronTable& tb,
-                                                  long long row, int np,
-                                                  int lane) {
+__device__ __forceinline__ bool kron_reserve(const KronTable& tb,
+                                             long long row, int np,
+                                             int lane) {
   long long base = 0;
   if (lane == 0)
     base = (long long)atomicAdd((unsigned long long*)tb.count,
@@ -469,13 +482,14 @@ __device__ __forceinline__ long long kron_reserve(const KronTable& tb,
     // entries that would fit stay marked empty
     for (long long i = base + lane; i < tb.cap && i < base + np; i += kWave)
       tb.part[i].row = -1;
-    return -1;
+    return false;
   }
   for (int i = lane; i < np; i += kWave) {
     tb.part[base + i].row = row;
     tb.part[base + i].k = i;
+    tb.part[base + i].done = 0;
   }
-  return base;
+  return true;
 }
 
 // The sums of part k of a row's pass PASS window, by one wave: pass 1 sum
@@ -541,8 +555,8 @@ __attribute__((amdgpu_waves_per_eu(3))) void k_kron(Work wk, ipp_sources src,
     // ---- pass 1: first moment over the search ellipse ------------------
     const KronWin sw = search_window(fr, r, search);
     if (sw.npx > kKronBigPx) {             // both passes in parts
-      const long long base = kron_reserve(t1, row, kron_parts(sw.npx), lane);
-      if (lane == 0) area[row] = (double)base;
+      const bool listed = kron_reserve(t1, row, kron_parts(sw.npx), lane);
+      if (lane == 0) flags[row] = listed ? 0u : kKronLeft1;
       continue;
     }
     double num = 0.0, den = 0.0;
@@ -557,11 +571,10 @@ __attribute__((amdgpu_waves_per_eu(3))) void k_kron(Work wk, ipp_sources src,
       fl |= 4u;
     const KronWin kw = kron_window(fr, r, R);
     if (kw.npx > kKronBigPx) {             // pass 2 in parts
-      const long long base = kron_reserve(t2, row, kron_parts(kw.npx), lane);
+      const bool listed = kron_reserve(t2, row, kron_parts(kw.npx), lane);
       if (lane == 0) {
         kron[row] = R;
-        flags[row] = fl;
-        area[row] = (double)base;
+        flags[row] = listed ? fl : fl | kKronLeft2;
       }
       continue;
     }
@@ -581,16 +594,58 @@ __attribute__((amdgpu_waves_per_eu(3))) void k_kron(Work wk, ipp_sources src,
   }
 }
 
-// The listed parts of one pass, a wave each.
+// The listed parts of one pass, a wave each; the wave that sums the last of a
+// row's parts finishes the row: its lane l adds the parts l, l + 64, .. in
+// order, then the lanes are added.  Pass 1 gives the Kron radius and lists the
+// row's pass-2 parts, pass 2 flux and area.  Rows that found the table full
+// (there are none unless the count exceeds it) are taken one after the other
+// by a workgroup, its waves summing their parts in turn; the additions are
+// the same.
+// A launch is bound by the longest part: 2048 pixels, 32 us for all parts of
+// four 4096 x 4096 frames (4096 pixels: 59 us); windows over 4096 pixels go in
+// parts, one wavefront takes about 20 us for such a window.  Finishing the
+// rows in two kernels of their own cost every call two launches more (20 rows
+// of a 256 x 256 frame: 38 against 33.5 us) and read every row's windows again
+// (13 us on the four frames; 5 here).  Pass 1 takes 84 registers: at eight
+// wavefronts a SIMD it spills (33 against 30 us, both with the release).
 template <int PASS>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(PASS == 2 ? 3 : 8))) void k_kron_parts(
-    Work wk, ipp_sources src, const double* mom, double search, KronTable tb,
-    const double* kron) {
+__attribute__((amdgpu_waves_per_eu(PASS == 2 ? 3 : 4))) void k_kron_parts(
+    Work wk, ipp_sources src, const double* mom, double kfac, double rmin,
+    double search, KronTable tb, KronTable next, double* kron, double* flux,
+    double* area, uint32_t* flags) {
   __shared__ int cut_lds[kWaves][PASS == 2 ? kCut : 1];
+  __shared__ uint64_t left;
+  __shared__ double part[2][kWave];
+  __shared__ int pedge;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int lane = threadIdx.x & (kWave - 1);
-  const long long n = *tb.count < tb.cap ? *tb.count : tb.cap;
+  const long long count = *tb.count;
+  // row's result from the sums over its parts (one wave)
+  auto finish = [&](long long row, const KronRow& r, const FrameDev& fr,
+                    double s0, double s1, bool edge) {
+    s0 = wave_sum(s0);
+    s1 = wave_sum(s1);
+    if constexpr (PASS == 1) {
+      uint32_t fl = 0;
+      const double R = kron_radius(s0, s1, kfac, rmin, &fl);
+      if (!(r.cx >= -0.5 && r.cx <= (double)fr.w - 0.5 && r.cy >= -0.5 &&
+            r.cy <= (double)fr.h - 0.5))
+        fl |= 4u;
+      const int np = kron_parts(kron_window(fr, r, R).npx);
+      const bool listed = np == 0 || kron_reserve(next, row, np, lane);
+      if (lane == 0) {
+        kron[row] = R;
+        flags[row] = listed ? fl : fl | kKronLeft2;
+        if (np == 0) flux[row] = area[row] = 0.0;   // nothing left to sum
+      }
+    } else if (lane == 0) {
+      flux[row] = s0;
+      area[row] = s1;
+      flags[row] = (flags[row] & ~kKronLeft2) | (edge ? 4u : 0u);  // off frame
+    }
+  };
+  const long long n = count < tb.cap ? count : tb.cap;
   for (long long i = blockIdx.x * (long long)kWaves + wv; i < n;
        i += (long long)gridDim.x * kWaves) {
     const long long row = tb.part[i].row;
@@ -600,165 +655,95 @@ __attribute__((amdgpu_waves_per_eu(PASS == 2 ? 3 : 8))) void k_kron_parts(
     const double R = PASS == 2 ? kron[row] : 0.0;
     const KronWin kw =
         PASS == 1 ? search_window(fr, r, search) : kron_window(fr, r, R);
+    const int k = tb.part[i].k, np = kron_parts(kw.npx);
+    KronPart* first = tb.part + (i - k);
     double s0, s1;
     bool edge;
-    kron_part<PASS>(fr, r, R, search, kw, tb.part[i].k, lane, cut_lds[wv],
-                    s0, s1, edge);
+    kron_part<PASS>(fr, r, R, search, kw, k, lane, cut_lds[wv], s0, s1, edge);
+    int before = 0;
     if (lane == 0) {
-      tb.part[i].s0 = s0;
-      tb.part[i].s1 = s1;
-      tb.part[i].edge = edge;
+      // The sums are performed (stores past the L2, and a wait for them)
+      // before the part is counted, and those of a full count are loaded past
+      // the caches after it: the parts of a row may be summed on several
+      // XCDs.  (A device-scope release in their place writes the L2 back,
+      // once a part: 30 against 21 us for pass 1 of four 4096^2 frames.)
+      part_store(&tb.part[i].s0, s0);
+      part_store(&tb.part[i].s1, s1);
+      if (edge)
+        __hip_atomic_fetch_or(&first->done, kPartEdge, __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_AGENT);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_s_waitcnt(0);
+      before = __hip_atomic_fetch_add(&first->done, 1, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
     }
+    before = __builtin_amdgcn_readfirstlane(before);
+    if ((before & (kPartEdge - 1)) != np - 1) continue;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    s0 = s1 = 0.0;
+    for (int q = lane; q < np; q += kWave) {
+      s0 += part_load(&first[q].s0);
+      s1 += part_load(&first[q].s1);
+    }
+    finish(row, r, fr, s0, s1, (before & kPartEdge) != 0);
   }
-}
-
-// The parts bound a launch by the longest part: 2048 pixels, 32 us for all
-// parts of four 4096 x 4096 frames (4096 pixels: 59 us); windows over 4096
-// pixels go in parts, one wavefront takes about 20 us for such a window.
-// Finishes the rows whose pass PASS went in parts: a workgroup checks
-// kBigThreads rows at once (one per thread), then each such row has its
-// parts' sums added by one wave, lane l taking the parts l, l + 64, .. in
-// order.  A row without part entries is summed here, the workgroup's waves
-// taking its parts in turn; the additions are the same.  Pass 1 gives the
-// Kron radius and lists the row's pass-2 parts, pass 2 flux and area.
-template <int PASS>
-__global__ __launch_bounds__(kBigThreads) void k_kron_finish(
-    Work wk, ipp_sources src, const double* mom, double kfac, double rmin,
-    double search, KronTable tb, KronTable next, double* kron, double* flux,
-    double* area, uint32_t* flags) {
-  constexpr int kBigWaves = kBigThreads / kWave;
-  __shared__ int cut_lds[kBigWaves][PASS == 2 ? kCut : 1];
-  __shared__ int list[kBigThreads];
-  __shared__ int nlist;
-  __shared__ double part[2][kWave];
-  __shared__ int pedge;
-  if (threadIdx.x == 0) nlist = 0;
-  __syncthreads();
-  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  const int lane = threadIdx.x & (kWave - 1);
+  if (count <= tb.cap) return;
+  // ---- rows that found the table full -----------------------------------
   long long nrows = src.capacity;
   if (src.n_total && *src.n_total < nrows) nrows = *src.n_total;
-  // row's result from the sums over its parts (one wave)
-  auto finish = [&](long long row, const KronRow& r, const FrameDev& fr,
-                    double s0, double s1, bool edge) {
-    s0 = wave_sum(s0);
-    s1 = wave_sum(s1);
-    edge = ballot(edge) != 0;
-    if constexpr (PASS == 1) {
-      uint32_t fl = 0;
-      const double R = kron_radius(s0, s1, kfac, rmin, &fl);
-      if (!(r.cx >= -0.5 && r.cx <= (double)fr.w - 0.5 && r.cy >= -0.5 &&
-            r.cy <= (double)fr.h - 0.5))
-        fl |= 4u;
-      const KronWin kw = kron_window(fr, r, R);
-      const long long base =
-          kron_reserve(next, row, kron_parts(kw.npx), lane);
-      if (lane == 0) {
-        kron[row] = R;
-        flags[row] = fl;
-        area[row] = (double)base;
-      }
-    } else if (lane == 0) {
-      flux[row] = s0;
-      area[row] = s1;
-      if (edge) flags[row] |= 4u;                       // off the frame
-    }
-  };
-  for (long long base = blockIdx.x * (long long)kBigThreads; base < nrows;
-       base += (long long)gridDim.x * kBigThreads) {
-    {
-      const long long row = base + threadIdx.x;
-      bool big = false;
-      if (row < nrows) {
-        const KronRow r = kron_row(wk, src, mom, row);
-        if (r.ok) {
-          const FrameDev& fr = wk.frames[r.f];
-          big = search_window(fr, r, search).npx > kKronBigPx ||
-                (PASS == 2 &&
-                 kron_window(fr, r, kron[row]).npx > kKronBigPx);
-        }
-      }
-      if (big) list[atomicAdd(&nlist, 1)] = (int)threadIdx.x;
+  for (long long base = blockIdx.x * (long long)kWave; base < nrows;
+       base += (long long)gridDim.x * kWave) {
+    __syncthreads();
+    if (wv == 0) {
+      const long long row = base + lane;
+      const uint64_t m = ballot(
+          row < nrows && (flags[row] & (PASS == 1 ? kKronLeft1 : kKronLeft2)));
+      if (lane == 0) left = m;
     }
     __syncthreads();
-    const int nb = nlist;
-    bool left = false;                // a listed row without part entries
-    for (int i = wv; i < nb; i += kBigWaves) {
-      const long long row = base + list[i];
-      const long long first = (long long)area[row];
-      if (first < 0) {
-        left = true;
-        continue;
-      }
+    for (uint64_t todo = left; todo; todo &= todo - 1) {
+      const long long row = base + __builtin_ctzll(todo);
       const KronRow r = kron_row(wk, src, mom, row);
       const FrameDev fr = wk.frames[r.f];
-      const KronWin kw = PASS == 1 ? search_window(fr, r, search)
-                                   : kron_window(fr, r, kron[row]);
+      const double R = PASS == 2 ? kron[row] : 0.0;
+      const KronWin kw =
+          PASS == 1 ? search_window(fr, r, search) : kron_window(fr, r, R);
       const int np = kron_parts(kw.npx);
-      double s0 = 0.0, s1 = 0.0;
-      bool edge = false;
-      for (int k = lane; k < np; k += kWave) {
-        const KronPart& q = tb.part[first + k];
-        s0 += q.s0;
-        s1 += q.s1;
-        edge |= PASS == 2 && q.edge != 0;
-      }
-      finish(row, r, fr, s0, s1, edge);
-      if (lane == 0) list[i] = -1;
-    }
-    if (__syncthreads_or(left)) {
-      for (int i = 0; i < nb; ++i) {
-        if (list[i] < 0) continue;
-        const long long row = base + list[i];
-        const KronRow r = kron_row(wk, src, mom, row);
-        const FrameDev fr = wk.frames[r.f];
-        const double R = PASS == 2 ? kron[row] : 0.0;
-        const KronWin kw =
-            PASS == 1 ? search_window(fr, r, search) : kron_window(fr, r, R);
-        const int np = kron_parts(kw.npx);
-        double t0 = 0.0, t1 = 0.0;
-        if (threadIdx.x == 0) pedge = 0;
-        for (int k0 = 0; k0 < np; k0 += kWave) {
-          __syncthreads();
-          for (int k = k0 + wv; k < min(np, k0 + kWave); k += kBigWaves) {
-            double s0, s1;
-            bool edge;
-            kron_part<PASS>(fr, r, R, search, kw, k, lane, cut_lds[wv], s0,
-                            s1, edge);
-            if (lane == 0) {
-              part[0][k - k0] = s0;
-              part[1][k - k0] = s1;
-              if (edge) atomicOr(&pedge, 1);
-            }
-          }
-          __syncthreads();
-          if (k0 + lane < np) {
-            t0 += part[0][lane];
-            t1 += part[1][lane];
+      double t0 = 0.0, t1 = 0.0;
+      if (threadIdx.x == 0) pedge = 0;
+      for (int k0 = 0; k0 < np; k0 += kWave) {
+        __syncthreads();
+        for (int k = k0 + wv; k < min(np, k0 + kWave); k += kWaves) {
+          double s0, s1;
+          bool edge;
+          kron_part<PASS>(fr, r, R, search, kw, k, lane, cut_lds[wv], s0, s1,
+                          edge);
+          if (lane == 0) {
+            part[0][k - k0] = s0;
+            part[1][k - k0] = s1;
+            if (edge) atomicOr(&pedge, 1);
           }
         }
         __syncthreads();
-        if (wv == 0) finish(row, r, fr, t0, t1, pedge != 0);
-        __syncthreads();
+        if (k0 + lane < np) {
+          t0 += part[0][lane];
+          t1 += part[1][lane];
+        }
       }
+      __syncthreads();
+      if (wv == 0) finish(row, r, fr, t0, t1, pedge != 0);
+      __syncthreads();
     }
-    __syncthreads();
-    if (threadIdx.x == 0) nlist = 0;
-    __syncthreads();
   }
 }
 
 template __global__ void k_kron_parts<1>(Work, ipp_sources, const double*,
-                                         double, KronTable, const double*);
+                                         double, double, double, KronTable,
+                                         KronTable, double*, double*, double*,
+                                         uint32_t*);
 template __global__ void k_kron_parts<2>(Work, ipp_sources, const double*,
-                                         double, KronTable, const double*);
-template __global__ void k_kron_finish<1>(Work, ipp_sources, const double*,
-                                          double, double, double, KronTable,
-                                          KronTable, double*, double*,
-                                          double*, uint32_t*);
-template __global__ void k_kron_finish<2>(Work, ipp_sources, const double*,
-                                          double, double, double, KronTable,
-                                          KronTable, double*, double*,
-                                          double*, uint32_t*);
+                                         double, double, double, KronTable,
+                                         KronTable, double*, double*, double*,
+                                         uint32_t*);
 
 }  // namespace ipp

@@ -152,14 +152,13 @@ __global__ void k_db_diag(const int64_t* tot, int64_t pool_units,
 
 // AUTO (Kron) photometry: one wavefront per row (k_kron.hip); windows of
 // more than kKronBigPx pixels go in parts of kKronPart pixels: k_kron lists
-// them, then k_kron_parts<1>, k_kron_finish<1> (pass 1 of the rows whose
-// search window is large), k_kron_parts<2>, k_kron_finish<2>.
+// them, then k_kron_parts<1> (pass 1 of the rows whose search window is
+// large) and k_kron_parts<2>.
 constexpr int kKronBigPx = 4096;
 constexpr int kKronPart = 2048;
-constexpr int kBigThreads = 512;
 struct KronPart {
   int64_t row;           // -1: not used
-  int32_t k, edge;       // part of the row; a member off the frame
+  int32_t k, done;       // part of the row; of its first: parts summed
   double s0, s1;         // the part's two sums
 };
 struct KronTable {
@@ -173,12 +172,9 @@ __global__ void k_kron(Work wk, ipp_sources src, const double* mom,
                        uint32_t* flags);
 template <int PASS>
 __global__ void k_kron_parts(Work wk, ipp_sources src, const double* mom,
-                             double search, KronTable tb, const double* kron);
-template <int PASS>
-__global__ void k_kron_finish(Work wk, ipp_sources src, const double* mom,
-                              double kfac, double rmin, double search,
-                              KronTable tb, KronTable next, double* kron,
-                              double* flux, double* area, uint32_t* flags);
+                             double kfac, double rmin, double search,
+                             KronTable tb, KronTable next, double* kron,
+                             double* flux, double* area, uint32_t* flags);
 
 // Stamp convolution and subtraction of the batch's `stamps` stamps (the
 // descriptors already on the device).
