@@ -469,6 +469,10 @@ ipp_status ipp_source_moments(void* ctx, const ipp_frame* frames, int32_t n,
  *  - rows with unusable moments (det <= 0 or not finite) get NaN (flag 1).
  * Outputs (device, per row): kron (R), flux, area, flags.  ap nullable:
  * defaults kron_factor 2.5, kron_min 3.5, search 6.
+ * Windows of more than 4096 pixels are shared out over the device by a list
+ * in the workspace beyond the required part, 64 bytes per 2048 pixels of such
+ * windows; without room for it the results are the same, a window of
+ * millions of pixels takes longer (one workgroup).
  */
 typedef struct ipp_auto_params {
   double kron_factor;     /* k in R = k r1 (2.5)                          */

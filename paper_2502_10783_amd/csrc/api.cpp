@@ -1705,7 +1705,7 @@ ipp_status ipp_photometry_auto(void* ctx, const ipp_frame* frames, int32_t n,
   const KronTable t2 = {w.counters + 1, parts + cap, cap};
   const dim3 b(kBlock);
   const dim3 gp(std::max(grid_for(cap, kWaves, 8 * c->n_cu),
-                         grid_for(src->capacity, kWave, 4 * c->n_cu)));
+                         grid_for(src->capacity, 1, 8 * c->n_cu)));
   IPP_LAUNCH(c, s, "k_kron",
              hipLaunchKernelGGL(k_kron,
                                 dim3(grid_for(src->capacity, kRowWaves,
