@@ -546,14 +546,15 @@ __device__ __forceinline__ long long nrec_used(const Work& wk) {
 }
 
 namespace {
-// Frame offsets, candidate count and diagnostics (thread i of n), once the
-// rows are scanned.
+// Frame offsets (first(f): frame f's first candidate), candidate count and
+// diagnostics (thread i of n).
+template <class F>
 __device__ __forceinline__ void table_heads(const Work& wk,
                                             const ipp_sources& src,
                                             int64_t* diag, long long total,
-                                            int i, int n) {
+                                            int i, int n, F&& first) {
   for (int f = i; f < wk.nframes; f += n)
-    src.frame_offsets[f] = wk.row_start[wk.frames[f].row0];
+    src.frame_offsets[f] = first(wk.frames[f]);
   if (i == 0) {
     src.frame_offsets[wk.nframes] = total;
     if (src.n_total) *src.n_total = total;
@@ -567,8 +568,7 @@ __device__ __forceinline__ void table_heads(const Work& wk,
 }
 
 // Exclusive scan of the row counts by one workgroup of kScanThreads, 4 rows
-// per thread and round; returns the total.  Counts are read past the L1
-// (another kernel phase of the same workgroup may have added to them).
+// per thread and round; returns the total.
 constexpr int kScanWaves = kScanThreads / kWave;
 __device__ __forceinline__ int scan_rows(const Work& wk, int* red) {
   int carry = 0;
@@ -577,7 +577,7 @@ __device__ __forceinline__ int scan_rows(const Work& wk, int* red) {
     const int j0 = r0 + 4 * (int)threadIdx.x;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      v[i] = j0 + i < wk.total_rows ? gload(&wk.row_count[j0 + i]) : 0;
+      v[i] = j0 + i < wk.total_rows ? wk.row_count[j0 + i] : 0;
       s += v[i];
     }
     int tot;
@@ -593,32 +593,17 @@ __device__ __forceinline__ int scan_rows(const Work& wk, int* red) {
 }
 
 // A step between two phases of one workgroup on global memory: every access
-// of the workgroup so far has been performed.
+// of the workgroup so far has been performed, and the loads after it do not
+// find what the L1 held before.
 __device__ __forceinline__ void phase_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
-// A record other threads of the workgroup may have updated (read past the
-// L1).
-__device__ __forceinline__ Rec load_rec(const Rec* q) {
-  Rec R;
-  R.minidx = gload(&q->minidx);
-  R.npix = gload(&q->npix);
-  R.xmin = gload(&q->xmin);
-  R.xmax = gload(&q->xmax);
-  R.ymin = gload(&q->ymin);
-  R.ymax = gload(&q->ymax);
-  R.frame = gload(&q->frame);
-  R.pad = 0;
-  return R;
-}
-
-// Folds record r into its root; true if r is a root.
-__device__ __forceinline__ bool fold_record(const Work& wk, int r) {
-  const int root = gfind(wk.rparent, r);
-  if (root == r) return true;
+// Folds record r, not a root, into its root.
+__device__ __forceinline__ void fold_record(const Work& wk, int r, int root) {
   wk.rparent[r] = root;
   const Rec R = wk.recs[r];
   Rec* T = &wk.recs[root];
@@ -628,20 +613,15 @@ __device__ __forceinline__ bool fold_record(const Work& wk, int r) {
   atomicMax(&T->xmax, R.xmax);
   atomicMin(&T->ymin, R.ymin);
   atomicMax(&T->ymax, R.ymax);
-  return false;
 }
 
-// Label and table row of a candidate that is the `rank`-th of its row's
-// `cnt` candidates, whose first is number s0 of the batch; f0: the number
-// of its frame's first.
-__device__ __forceinline__ void put_row(const Work& wk, ipp_sources& src,
-                                        const Rec& R, int r, long long out,
-                                        int f0) {
-  const int label = (int)(out - f0) + 1;
-  wk.rlabel[r] = label;
+// Table row of a candidate, number `out` of the batch; f0: the number of its
+// frame's first.
+__device__ __forceinline__ void put_row(ipp_sources& src, const Rec& R,
+                                        long long out, int f0) {
   if (out < src.capacity) {
     src.frame[out] = R.frame;
-    src.label[out] = label;
+    src.label[out] = (int)(out - f0) + 1;
     src.npix[out] = R.npix;
     src.xmin[out] = R.xmin;
     src.xmax[out] = R.xmax;
@@ -655,7 +635,8 @@ __global__ __launch_bounds__(kBlock) void k_resolve(Work wk, ipp_params p) {
   const long long n = nrec_used(wk);
   for (long long r = blockIdx.x * (long long)kBlock + threadIdx.x; r < n;
        r += (long long)gridDim.x * kBlock) {
-    fold_record(wk, (int)r);
+    const int root = gfind(wk.rparent, (int)r);
+    if (root != r) fold_record(wk, (int)r, root);
   }
 }
 
@@ -735,7 +716,8 @@ __global__ void k_clear(Work wk) {
 
 __global__ void k_frame_offsets(Work wk, ipp_sources src, int64_t* diag) {
   table_heads(wk, src, diag, wk.counters[3],
-              blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+              blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x,
+              [&](const FrameDev& fr) { return wk.row_start[fr.row0]; });
 }
 
 // The scan of a batch of at most kScanRows rows in one launch (one workgroup,
@@ -747,61 +729,132 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_rows(Work wk,
   const int total = scan_rows(wk, red);
   phase_sync();
   if (threadIdx.x == 0) wk.counters[3] = total;
-  table_heads(wk, src, diag, total, threadIdx.x, kScanThreads);
+  table_heads(wk, src, diag, total, threadIdx.x, kScanThreads,
+              [&](const FrameDev& fr) { return wk.row_start[fr.row0]; });
 }
 
 // Everything between the tile borders and the label map for a batch of at
-// most kSmallTiles tiles, by one workgroup: fold, count, scan, offsets,
-// scatter, rank, labels.  The phases are microseconds each on a few hundred
-// records, less than the launch of a kernel; on more tiles one workgroup's
-// loops over the records cost more than the launches saved (a pass on a
-// 512 x 512 frame, 64 tiles, with and without this kernel: 162 and 167 us; on
-// 768 x 768, 144 tiles, 174 and 173; on 1024 x 1024, 256 tiles, 210 and 200).
+// most kSmallTiles tiles, by one workgroup: fold, number, label.  A candidate's
+// number is the count of candidates whose first pixel comes before its own,
+// read from a bitmap of the batch's pixels in LDS; nothing is sorted, and no
+// row of candidates is walked.  Every phase is a chain of two or three loads
+// for a record, so a thread has kSmallAhead records in flight (8: the same
+// up to 12,000 records).  One 512 x 512 frame: 10 us for 93 candidates, 25
+// for 5,700, 42 for 12,200; the six kernels that larger batches take, on a
+// 600 x 600 frame, 21 us for 145 and 38 for 15,200.  Rows of candidates sorted
+// by walking them took a pass on the 512 x 512 frame from 235 to 429 us at
+// 12,200 candidates (219 so).  One workgroup's accesses are the bound: of
+// isolated pixels, more than noise can give, 32,800 take 139 us a detection
+// and 65,500 take 226, against 138 and 199 over the whole device.
+// kSmallTiles: the bitmap and its counts are 96 KB of the 160 KB of LDS; a
+// pass on 768 x 768 pixels, 144 tiles, took as long either way.
+constexpr int kSmallWords = kSmallTiles * 4096 / 32;
+constexpr int kSmallAhead = 4;
 __global__ __launch_bounds__(kScanThreads) void k_number_small(
     Work wk, ipp_params p, ipp_sources src, int64_t* diag) {
+  __shared__ uint32_t bits[kSmallWords];   // first pixels of the candidates
+  __shared__ int before[kSmallWords];      // candidates before each word
   __shared__ int red[kScanWaves];
+  constexpr int U = kSmallAhead, kStep = U * kScanThreads;
+  constexpr int kPer = (kSmallWords + kScanThreads - 1) / kScanThreads;
   const long long used = wk.counters[0];
   const int n = (int)(used < wk.rec_cap ? used : wk.rec_cap);
   const int t = threadIdx.x;
-  for (int r = t; r < n; r += kScanThreads) fold_record(wk, r);
-  phase_sync();
-  for (int r = t; r < n; r += kScanThreads) {
-    if (gload(&wk.rparent[r]) != r) continue;
-    const Rec* q = wk.recs + r;
-    if (gload(&q->npix) < p.min_area) continue;
-    const FrameDev& fr = wk.frames[q->frame];
-    atomicAdd(&wk.row_count[fr.row0 + gload(&q->minidx) / fr.w], 1);
+  for (int i = t; i < kSmallWords; i += kScanThreads) bits[i] = 0;
+  for (int r0 = t; r0 < n; r0 += kStep) {
+    int q[U], root[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      q[u] = gload(&wk.rparent[min(r0 + u * kScanThreads, n - 1)]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) root[u] = gload(&wk.rparent[q[u]]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = r0 + u * kScanThreads;
+      if (r >= n || q[u] == r) continue;
+      if (root[u] != q[u]) root[u] = gfind(wk.rparent, root[u]);
+      fold_record(wk, r, root[u]);
+    }
   }
   phase_sync();
-  const int total = scan_rows(wk, red);
-  phase_sync();
+  for (int r0 = t; r0 < n; r0 += kStep) {
+    int root[U], np[U], first[U], f[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = min(r0 + u * kScanThreads, n - 1);
+      const Rec* q = wk.recs + r;
+      root[u] = wk.rparent[r];
+      np[u] = q->npix;
+      first[u] = q->minidx;
+      f[u] = q->frame;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = r0 + u * kScanThreads;
+      if (r >= n || root[u] != r || np[u] < p.min_area) continue;
+      const int b = (int)wk.frames[f[u]].pix0 + first[u];
+      atomicOr(&bits[b >> 5], 1u << (b & 31));
+    }
+  }
+  __syncthreads();
+  int own = 0, total;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int w = t * kPer + i;
+    if (w < kSmallWords) own += __popc(bits[w]);
+  }
+  int at = block_exclusive_scan<kScanWaves>(own, red, &total);
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int w = t * kPer + i;
+    if (w < kSmallWords) {
+      before[w] = at;
+      at += __popc(bits[w]);
+    }
+  }
+  __syncthreads();
+  // candidates whose first pixel lies before pixel b of the batch
+  auto number = [&](int b) {
+    return before[b >> 5] + __popc(bits[b >> 5] & ((1u << (b & 31)) - 1u));
+  };
+  auto first_of = [&](const FrameDev& fr) { return number((int)fr.pix0); };
   if (t == 0) wk.counters[3] = total;
-  table_heads(wk, src, diag, total, t, kScanThreads);
-  for (int r = t; r < n; r += kScanThreads) {
-    if (gload(&wk.rparent[r]) != r) continue;
-    const Rec* q = wk.recs + r;
-    if (gload(&q->npix) < p.min_area) continue;
-    const FrameDev& fr = wk.frames[q->frame];
-    const int g = fr.row0 + gload(&q->minidx) / fr.w;
-    const int slot = atomicAdd(&wk.row_cursor[g], 1);
-    wk.bucket[wk.row_start[g] + slot] = r;
+  table_heads(wk, src, diag, total, t, kScanThreads, first_of);
+  // Labels; the table rows of few candidates too, those of many (scattered
+  // stores to seven columns otherwise) in the order of the table below.
+  const bool many = total > kScanThreads;
+  for (int r0 = t; r0 < n; r0 += kStep) {
+    int root[U];
+    Rec R[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      root[u] = wk.rparent[min(r0 + u * kScanThreads, n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) R[u] = wk.recs[root[u]];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = r0 + u * kScanThreads;
+      if (r >= n || R[u].npix < p.min_area) continue;    // the label stays 0
+      const FrameDev& fr = wk.frames[R[u].frame];
+      const int out = number((int)fr.pix0 + R[u].minidx), f0 = first_of(fr);
+      wk.rlabel[r] = out - f0 + 1;
+      if (root[u] != r) continue;
+      if (many) wk.bucket[out] = r;
+      else put_row(src, R[u], out, f0);
+    }
   }
+  if (!many) return;
   phase_sync();
-  for (int e = t; e < total; e += kScanThreads) {
-    const int r = gload(&wk.bucket[e]);
-    const Rec R = load_rec(wk.recs + r);
-    const FrameDev& fr = wk.frames[R.frame];
-    const int g = fr.row0 + R.minidx / fr.w;
-    const int s0 = wk.row_start[g], cnt = gload(&wk.row_count[g]);
-    int rank = 0;
-    for (int i = 0; i < cnt; ++i)
-      rank += gload(&wk.recs[gload(&wk.bucket[s0 + i])].minidx) < R.minidx;
-    put_row(wk, src, R, r, (long long)s0 + rank, wk.row_start[fr.row0]);
-  }
-  phase_sync();
-  for (int r = t; r < n; r += kScanThreads) {
-    const int root = gload(&wk.rparent[r]);
-    if (root != r) wk.rlabel[r] = gload(&wk.rlabel[root]);
+  for (int e0 = t; e0 < total; e0 += kStep) {
+    Rec R[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      R[u] = wk.recs[wk.bucket[min(e0 + u * kScanThreads, total - 1)]];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * kScanThreads;
+      if (e < total) put_row(src, R[u], e, first_of(wk.frames[R[u].frame]));
+    }
   }
 }
 
@@ -832,7 +885,10 @@ __global__ __launch_bounds__(kBlock) void k_rank(Work wk, ipp_params p,
     int rank = 0;
     for (int i = 0; i < cnt; ++i)
       rank += wk.recs[wk.bucket[s0 + i]].minidx < R.minidx;
-    put_row(wk, src, R, r, (long long)s0 + rank, wk.row_start[fr.row0]);
+    const long long out = (long long)s0 + rank;
+    const int f0 = wk.row_start[fr.row0];
+    wk.rlabel[r] = (int)(out - f0) + 1;
+    put_row(src, R, out, f0);
   }
 }
 

@@ -58,7 +58,7 @@ __global__ void k_clear(Work wk);
 __global__ void k_frame_offsets(Work wk, ipp_sources src, int64_t* diag);
 constexpr int kScanThreads = 1024;  // threads of the one-workgroup kernels
 constexpr int kScanRows = 16384;    // rows k_scan_rows takes
-constexpr int kSmallTiles = 96;    // detection tiles k_number_small takes
+constexpr int kSmallTiles = 96;     // detection tiles k_number_small takes
 __global__ void k_scan_rows(Work wk, ipp_sources src, int64_t* diag);
 __global__ void k_number_small(Work wk, ipp_params p, ipp_sources src,
                                int64_t* diag);
