@@ -90,7 +90,13 @@ __device__ __forceinline__ float map_pixel(float v, double lo, double inv,
 // Four consecutive values of a row of any alignment: one load or store (a
 // vector access to global memory needs only its elements' alignment).  Four
 // 4095 x 4093 frames, map and equalization: 380 us, 660 a value at a time.
-struct __attribute__((packed, aligned(4))) Float4 { float x, y, z, w; };
+typedef float Float4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ Float4 load4(const float* a) {
+  return *(const __attribute__((address_space(1))) Float4*)a;
+}
+__device__ __forceinline__ void store4(float* a, Float4 v) {
+  *(__attribute__((address_space(1))) Float4*)a = v;
+}
 
 // Row y of frame F: fn(v, out_row, x) with v a Float4 of columns x..x+3, or a
 // float of column x for the last w % 4.  Two groups per thread are loaded
@@ -101,17 +107,16 @@ __device__ __forceinline__ void row_elements(const GrayFrame& F, int y,
   const float* in = F.pix + (int64_t)y * F.pitch;
   float* out = F.out ? F.out + (int64_t)y * F.w : nullptr;
   const int n4 = F.w >> 2;
-  const Float4* in4 = (const Float4*)in;
   int i = threadIdx.x;
   for (; i + kBlock < n4; i += 2 * kBlock) {
-    const Float4 a = in4[i], b = in4[i + kBlock];
+    const Float4 a = load4(in + 4 * i), b = load4(in + 4 * (i + kBlock));
     fn(a, out, 4 * i);
     fn(b, out, 4 * (i + kBlock));
   }
-  if (i < n4) fn(in4[i], out, 4 * i);
+  if (i < n4) fn(load4(in + 4 * i), out, 4 * i);
   // the row's end (by the last threads instead: 392 against 380 us)
   const int xt = (n4 << 2) + (int)threadIdx.x;
-  if (xt < F.w) fn(in[xt], out, xt);
+  if (xt < F.w) fn(gld(in + xt), out, xt);
 }
 
 }  // namespace
@@ -328,9 +333,9 @@ __global__ __launch_bounds__(kBlock) void k_gray_map(
         o.y = map_pixel(v.y, lo, inv, step, m);
         o.z = map_pixel(v.z, lo, inv, step, m);
         o.w = map_pixel(v.w, lo, inv, step, m);
-        *(Float4*)(out + x) = o;
+        store4(out + x, o);
       } else {
-        out[x] = map_pixel(v, lo, inv, step, m);
+        gst(out + x, map_pixel(v, lo, inv, step, m));
       }
     });
   }
@@ -572,9 +577,9 @@ __global__ __launch_bounds__(kBlock) void k_eq_map(const GrayFrame* frames,
       if constexpr (sizeof(v) == sizeof(Float4)) {
         Float4 o;
         o.x = eq(v.x); o.y = eq(v.y); o.z = eq(v.z); o.w = eq(v.w);
-        *(Float4*)(out + x) = o;
+        store4(out + x, o);
       } else {
-        out[x] = eq(v);
+        gst(out + x, eq(v));
       }
     });
   }
