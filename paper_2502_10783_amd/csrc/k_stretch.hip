@@ -5,6 +5,8 @@
 // binary64 block partials reduced in a fixed order by one workgroup.
 #include <mutex>
 
+#include <type_traits>
+
 #include "ipp_internal.h"
 #include "kernels.h"
 
@@ -165,6 +167,7 @@ __device__ __forceinline__ double log1p_pos(double y, const LogEntry* tab) {
 //   asinh(v / a) = sign(v) log1p((|v| + (r - a)) / a),
 // where r - a is corrected by the remainder v^2 - (r - a)(r + a), so that it
 // keeps its digits for |v| far below a.
+template <bool TINY>
 __device__ __forceinline__ void asinh_bwd_one(float x, float g, double a,
                                               double a2, double inv_a,
                                               double b, bool want_ab,
@@ -173,6 +176,10 @@ __device__ __forceinline__ void asinh_bwd_one(float x, float g, double a,
   if (!want_ab) {
     const float af = (float)a, bf = (float)b;
     *dv = g * (bf / sqrtf(af * af + x * x));
+    return;
+  }
+  if (TINY && x == 0.0f) {           // a^2 is zero, but 1 / r is 1 / a
+    *dv = g * (float)(b * inv_a);
     return;
   }
   const double xd = (double)x, gd = (double)g;
@@ -217,22 +224,31 @@ __global__ __launch_bounds__(kBlock) void k_asinh_bwd(const float* v,
   double pa = 0.0, pb = 0.0;
   const bool vec =
       (((uintptr_t)v | (uintptr_t)dy | (uintptr_t)dv) & 15) == 0;
-  for_elements(n, vec, [&](int64_t i, bool four) {
-    if (four) {
-      const float4 x = ((const float4*)v)[i];
-      const float4 g = ((const float4*)dy)[i];
-      float4 o;
-      asinh_bwd_one(x.x, g.x, a, a2, inv_a, b, want_ab, tab, &o.x, pa, pb);
-      asinh_bwd_one(x.y, g.y, a, a2, inv_a, b, want_ab, tab, &o.y, pa, pb);
-      asinh_bwd_one(x.z, g.z, a, a2, inv_a, b, want_ab, tab, &o.z, pa, pb);
-      asinh_bwd_one(x.w, g.w, a, a2, inv_a, b, want_ab, tab, &o.w, pa, pb);
-      if (dv) ((float4*)dv)[i] = o;
-    } else {
-      float o;
-      asinh_bwd_one(v[i], dy[i], a, a2, inv_a, b, want_ab, tab, &o, pa, pb);
-      if (dv) dv[i] = o;
-    }
-  });
+  auto element = [&](auto tiny, float x, float g, float* o) {
+    asinh_bwd_one<tiny.value>(x, g, a, a2, inv_a, b, want_ab, tab, o, pa, pb);
+  };
+  auto walk = [&](auto tiny) {
+    for_elements(n, vec, [&](int64_t i, bool four) {
+      if (four) {
+        const float4 x = ((const float4*)v)[i];
+        const float4 g = ((const float4*)dy)[i];
+        float4 o;
+        element(tiny, x.x, g.x, &o.x);
+        element(tiny, x.y, g.y, &o.y);
+        element(tiny, x.z, g.z, &o.z);
+        element(tiny, x.w, g.w, &o.w);
+        if (dv) ((float4*)dv)[i] = o;
+      } else {
+        float o;
+        element(tiny, v[i], dy[i], &o);
+        if (dv) dv[i] = o;
+      }
+    });
+  };
+  // a below 1.5e-162: a loop of its own (the test in every element's way:
+  // 289 against 285 us forward and backward)
+  if (a2 == 0.0) walk(std::true_type{});
+  else walk(std::false_type{});
   if (!want_ab) return;
   pa = block_sum(pa, red) * (-b * inv_a);
   pb = block_sum(pb, red);
