@@ -1598,7 +1598,16 @@ ipp_status ipp_deblend(void* ctx, const ipp_frame* frames, int32_t n,
                                 p->connectivity, dp->nthresh, dp->clean,     \
                                 dp->mincont, dp->clean_param, cnt, QUEUE,    \
                                 big, tot + 4))
-  {
+  if (rows <= kDbAllRows) {
+    IPP_LAUNCH(c, s, "k_db_all",
+               hipLaunchKernelGGL(k_db_all,
+                                  dim3(grid_for(rows, 1, c->n_cu)),
+                                  dim3(8 * kWave), 0, s, w, *cand, off, tot,
+                                  pool, pool_units, p->det_nsigma,
+                                  p->connectivity, dp->nthresh, dp->clean,
+                                  dp->mincont, dp->clean_param, cnt, tot + 3,
+                                  tot + 6, queue, big, tot + 4));
+  } else {
     Fork fork(c, s);
     IPP_DB(k_db_large, kDbLargePerCu, 8 * kWave, tot + 3, fork.side);
     IPP_DB(k_db_mid, kDbMidPerCu, 4 * kWave, tot + 6, s);

@@ -8,6 +8,7 @@
 //                more than 64 bits, a workgroup of eight wavefronts each
 //   k_db_mid     boxes over kDbSmallBox pixels, a workgroup of four each
 //   k_db_small   the other candidates, a wavefront each
+//   k_db_all     the three in one launch, for tables of up to 2048 rows
 //   k_db_write   a wavefront per candidate: object ids into the object
 //                maps, the objects' rows (frame, label, parent, pixel
 //                count, box)
@@ -1083,17 +1084,16 @@ __device__ __forceinline__ int deblend_row(
 
 // Candidates of class CLS, one per group, taken from the queue counter: class
 // 0 in row order, the others from k_db_need's list (class 2 from its front,
-// class 1 from its back).
+// class 1 from its back).  The group is number gi of ng.
 template <int NW, int CAP, int CLS>
 __device__ __forceinline__ void db_groups(
-    Work wk, ipp_sources cand, const int64_t* off, const int64_t* tot,
-    char* pool, int64_t pool_units, double nsigma, int conn, int nthresh,
-    int clean, double mincont, double kc, int64_t* cnt, int64_t* queue,
-    const int32_t* big, const int64_t* nbig) {
-  __shared__ DbLds<NW, CAP> lds;
-  __shared__ long long next_row;
+    const Work& wk, const ipp_sources& cand, const int64_t* off,
+    const int64_t* tot, char* pool, int64_t pool_units, double nsigma,
+    int conn, int nthresh, int clean, double mincont, double kc, int64_t* cnt,
+    int64_t* queue, const int32_t* big, const int64_t* nbig,
+    DbLds<NW, CAP>& lds, int gi, int ng) {
   Grp<NW> g;
-  g.tid = threadIdx.x;
+  g.tid = threadIdx.x % Grp<NW>::T;
   g.lane = threadIdx.x & (kWave - 1);
   g.wave = g.tid / kWave;
   g.red = lds.red;
@@ -1103,25 +1103,31 @@ __device__ __forceinline__ void db_groups(
   if (CLS == 0) {
     // the counts of the rows that need no deblending (beyond the table: 0;
     // single pixels, or every row when the pool is too small: 1)
-    for (long long r = blockIdx.x * (long long)Grp<NW>::T + threadIdx.x;
-         r <= cand.capacity; r += (long long)gridDim.x * Grp<NW>::T) {
+    for (long long r = gi * (long long)Grp<NW>::T + g.tid; r <= cand.capacity;
+         r += (long long)ng * Grp<NW>::T) {
       if (r >= n) cnt[r] = 0;
       else if (cand.npix[r] < 2 || !fits) cnt[r] = 1;
     }
   }
   if (!fits) return;
   const long long nlist = CLS == 0 ? n : (CLS == 2 ? nbig[0] : nbig[1]);
-  // class 0 takes its rows from several counters, a workgroup from one of
-  // them (thousands of short candidates queue up at one address: 12 ns each)
+  // class 0 takes its rows from several counters, a group from one of them
+  // (thousands of short candidates queue up at one address: 12 ns each)
   const int nq = CLS == 0 ? db_queues(cand.capacity) : 1;
-  const int qi = CLS == 0 ? blockIdx.x % nq : 0;
+  const int qi = CLS == 0 ? gi % nq : 0;
   while (true) {
+    long long r = 0;
     if (g.tid == 0)
-      next_row = (long long)atomicAdd(
+      r = (long long)atomicAdd(
           (unsigned long long*)queue + qi * kDbQueueStep, 1ull);
-    __syncthreads();
-    long long r = next_row;
-    __syncthreads();
+    if constexpr (NW == 1) {
+      r = __shfl(r, 0, kWave);
+    } else {
+      if (g.tid == 0) lds.red64[0] = r;
+      __syncthreads();
+      r = lds.red64[0];
+      __syncthreads();
+    }
     if (CLS == 0) r = r * nq + qi;
     if (r >= nlist) break;
     if (CLS == 2) r = big[r];
@@ -1162,9 +1168,10 @@ __device__ __forceinline__ void db_groups(
       char* pool, int64_t pool_units, double nsigma, int conn, int nthresh,  \
       int clean, double mincont, double kc, int64_t* cnt, int64_t* queue,    \
       const int32_t* big, const int64_t* nbig) {                             \
+    __shared__ DbLds<NW, CAP> lds;                                           \
     db_groups<NW, CAP, CLS>(wk, cand, off, tot, pool, pool_units, nsigma,    \
                             conn, nthresh, clean, mincont, kc, cnt, queue,   \
-                            big, nbig);                                      \
+                            big, nbig, lds, blockIdx.x, gridDim.x);          \
   }
 // Boxes of up to 512 pixels: a wavefront per candidate (13 KB of LDS each);
 // of up to 2048: a workgroup of four (51 KB); larger ones, in LDS up to 6144
@@ -1178,6 +1185,40 @@ IPP_DB_KERNEL(k_db_small, 1, kDbSmallBox, 0)
 IPP_DB_KERNEL(k_db_mid, 4, kDbMidBox, 1)
 IPP_DB_KERNEL(k_db_large, 8, kDbBigBox, 2)
 #undef IPP_DB_KERNEL
+
+// Everything in one launch, for tables of at most kDbAllRows rows: a workgroup
+// of eight wavefronts takes the candidates of the larger classes, then each of
+// its wavefronts small ones (2048 in flight on the device, so none waits).
+// Three launches, one of them forked to a side stream and joined, cost the
+// host more than a few candidates' work: 16 candidates of a 128 x 128 frame,
+// two levels, 226 us a call, 175 so (204 with two kernels on one stream); 218
+// of 300 x 300, 32 levels, 501 and 342.  Longer tables gain as well while their
+// large candidates are few (682 of 512 x 512 in a table of 5120: 487 and 317)
+// and lose where they are many (4,700 of a crowded 2048^2 frame: 639 and
+// 730), which only the device knows.
+__global__ __launch_bounds__(8 * kWave) void k_db_all(
+    Work wk, ipp_sources cand, const int64_t* off, const int64_t* tot,
+    char* pool, int64_t pool_units, double nsigma, int conn, int nthresh,
+    int clean, double mincont, double kc, int64_t* cnt, int64_t* queue2,
+    int64_t* queue1, int64_t* queue0, const int32_t* big,
+    const int64_t* nbig) {
+  __shared__ union {
+    DbLds<8, kDbBigBox> group;
+    DbLds<1, kDbSmallBox> wave[8];
+  } lds;
+  db_groups<8, kDbBigBox, 2>(wk, cand, off, tot, pool, pool_units, nsigma,
+                             conn, nthresh, clean, mincont, kc, cnt, queue2,
+                             big, nbig, lds.group, blockIdx.x, gridDim.x);
+  db_groups<8, kDbBigBox, 1>(wk, cand, off, tot, pool, pool_units, nsigma,
+                             conn, nthresh, clean, mincont, kc, cnt, queue1,
+                             big, nbig, lds.group, blockIdx.x, gridDim.x);
+  __syncthreads();                     // the group's LDS is the waves' now
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  db_groups<1, kDbSmallBox, 0>(wk, cand, off, tot, pool, pool_units, nsigma,
+                               conn, nthresh, clean, mincont, kc, cnt, queue0,
+                               big, nbig, lds.wave[wv], blockIdx.x * 8 + wv,
+                               gridDim.x * 8);
+}
 
 __global__ __launch_bounds__(kBlock) void k_db_zero(Work wk) {
   for (int f = blockIdx.y; f < wk.nframes; f += gridDim.y) {

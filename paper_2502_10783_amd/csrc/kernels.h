@@ -135,6 +135,14 @@ IPP_DB_DECLARE(k_db_small)
 IPP_DB_DECLARE(k_db_mid)
 IPP_DB_DECLARE(k_db_large)
 #undef IPP_DB_DECLARE
+// All three in one, for tables of at most kDbAllRows rows.
+constexpr int kDbAllRows = 2048;
+__global__ void k_db_all(Work wk, ipp_sources cand, const int64_t* off,
+                         const int64_t* tot, char* pool, int64_t pool_units,
+                         double nsigma, int conn, int nthresh, int clean,
+                         double mincont, double kc, int64_t* cnt,
+                         int64_t* queue2, int64_t* queue1, int64_t* queue0,
+                         const int32_t* big, const int64_t* nbig);
 __global__ void k_db_zero(Work wk);
 constexpr int kDbWriteThreads = 256;
 __global__ void k_db_write(Work wk, ipp_sources cand, const int64_t* off,
