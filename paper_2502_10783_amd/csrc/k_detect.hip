@@ -19,11 +19,14 @@ namespace ipp {
 
 namespace {
 
-// 32 tiles in a row to an XCD: what a tile writes and the next kernel reads
-// beside it, and the lines that neighbouring rows of odd widths share, stay in
-// one L2 (one 2048 x 3071 frame, k_tile_ccl 43 -> 39 us; a ragged batch of
-// ten, k_relabel 37 -> 33; 16 frames of 4096^2 1 %; 8, 16 and 64 in a row the
-// same within 2 %).
+// 32 tiles in a row to an XCD: the lines that neighbouring rows of odd widths
+// share stay in one L2.  It is single and odd frames that gain (one 2048 x 3071
+// frame, k_tile_ccl 42.8 -> 38.9 us; a ragged batch of ten, k_relabel 35.3 ->
+// 31.6 in one process, 33 in another); sixteen frames of 4096^2 take the same
+// (962 to 966 us and 266).  8, 16 and 64 in a row: the same within 2 %.  The
+// border unions and the background maps keep the plain order (9.3 against 8.8
+// and 20.1 against 19.4 us on the one frame, 70.2 against 69.7 on a field of
+// 10560^2).
 constexpr int kXcdTiles = 5;
 
 template <int TH, int TW, bool CONN8>
@@ -115,7 +118,7 @@ __device__ __forceinline__ void gunion(int32_t* parent, int a, int b) {
 template <int TH, int TW>
 __global__ __launch_bounds__(kBlock) void k_bkg_maps(Work wk, ipp_params p) {
   __shared__ SplineLds<TH, TW> S;
-  const int tile = xcd_item<kXcdTiles>(blockIdx.x, gridDim.x);
+  const int tile = blockIdx.x;
   const int f = find_frame(wk.frames, wk.nframes, tile, &FrameDev::dtile0);
   const FrameDev fr = wk.frames[f];
   const int lt = tile - fr.dtile0, ty = lt / fr.dtx, tx = lt - ty * fr.dtx;
@@ -491,7 +494,7 @@ __global__ __launch_bounds__(NT) void k_tile_ccl(Work wk, ipp_params p,
 template <int TH, int TW>
 __global__ __launch_bounds__((border_threads<TH, TW>())) void k_border(
     Work wk, ipp_params p) {
-  const int tile = xcd_item<kXcdTiles>(blockIdx.x, gridDim.x);
+  const int tile = blockIdx.x;
   const int f = find_frame(wk.frames, wk.nframes, tile, &FrameDev::dtile0);
   const FrameDev fr = wk.frames[f];
   const int lt = tile - fr.dtile0, ty = lt / fr.dtx, tx = lt - ty * fr.dtx;

@@ -475,7 +475,9 @@ namespace {
 constexpr int kWBins = 2048;       // level-1 bins: 32 per lane
 constexpr int kWSub = 1024;        // narrowing bins: 16 per lane
 constexpr int kWGather = 256;
-constexpr int kXcdRegions = 5;      // 32 regions in a row to an XCD
+// 32 regions in a row to an XCD (one 2048 x 3071 frame in regions of 32^2, 42.0
+// -> 39.7 us; sixteen 4096^2 frames the same)
+constexpr int kXcdRegions = 5;
 // registers whose comparisons are made ahead of the first branch on one (a
 // comparison's mask takes some 40 cycles to reach a branch)
 constexpr int kWAhead = 8;
