@@ -1,7 +1,7 @@
 // AUTO (Kron) photometry (Sec. 2.2.5 lists auto photometry among the
 // per-object measurements; Sec. 3.3 compares its magnitudes).
 //
-// One wavefront per object, four objects per workgroup.  The object's
+// One wavefront per object, in a workgroup of its own.  The object's
 // second moments (x2, y2, xy), regularised by the variance 1/12 of a
 // uniform unit pixel on each axis, give the quadratic form
 //   q(dx, dy) = (Y dx^2 + X dy^2 - 2 xy dx dy) / det,  det = X Y - xy^2,

@@ -1,8 +1,8 @@
 // Aperture photometry with a local sky annulus (Sec. 2.2.5: per-object
 // aperture photometry).
 //
-// One wavefront per source, four sources per workgroup, no workgroup
-// barriers.  The wave walks the source's window with the exact membership
+// One wavefront per source, no workgroup barriers (a workgroup has one source
+// in the photometry and the refinement, four in the backward).  The wave walks the source's window with the exact membership
 // predicates (from per-column and per-row distance tables), sums the
 // pixels wholly inside the aperture, appends every annulus value to its
 // LDS slice and lists every pixel cut by one of the three circles as one
@@ -221,7 +221,8 @@ struct ApLds {
   // counts are clamped round by round, so a round's appends stay inside the
   // array without a bound test per lane (the values lists likewise: the
   // count stays at most NS, and xs has kWave slots more).
-  // 16 bits: four workgroups of k_refine<512> fit a compute unit's LDS.
+  // 16 bits: sixteen wavefronts of k_refine<512>, 9.3 KB each, fit a compute
+  // unit's LDS.
   uint16_t tk[kCap + 2 * kWave];
   WinTablesT<NC> T;
 };
@@ -797,7 +798,7 @@ __attribute__((amdgpu_waves_per_eu(NS <= 512 ? 4 : 1))) void k_aperture_t(
 // variant of its own, so that the plain refinement keeps its registers).
 // Bound by vector instructions (3300 an evaluation, radii 5/8/12) and by the
 // latency of what each waits for, so wavefronts in flight count: four a SIMD
-// (128 registers, up to 15 spilled, 152 KB of LDS a compute unit) against
+// (128 registers, up to 12 spilled, 152 KB of LDS a compute unit) against
 // three: 8044 against 8829 us for 1.0e5 sources, 10 steps (four rows a
 // workgroup; 6945 with one).  With the atan
 // table in LDS, 32-bit task lists and three a SIMD it was 9900 us.
@@ -1052,7 +1053,7 @@ __device__ void aperture_bwd_one(const Work& wk, const ipp_params& p,
 
 }  // namespace
 
-// Four wavefronts a SIMD (128 registers, 126 KB of LDS a compute unit)
+// Four wavefronts a SIMD (128 registers, 134 KB of LDS a compute unit)
 // against three, both walking twice: 250 against 275 us for 16 frames of
 // 2048^2, 3.2e4 sources.
 template <int NS>
@@ -1061,7 +1062,6 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_aperture_bwd_t(
     Work wk, ipp_params p, ipp_sources src, const double* sky_lohi,
     const double* gF, double* dxy) {
   __shared__ BwLds<NS> L[kWaves];
-  __syncthreads();
   long long nrows = src.capacity;
   if (src.n_total && *src.n_total < nrows) nrows = *src.n_total;
   // wave index made provably uniform, so per-row loads are scalar

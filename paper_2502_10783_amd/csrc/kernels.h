@@ -46,7 +46,6 @@ __global__ void k_border(Work wk, ipp_params p);
 template <int TH, int TW>
 __global__ void k_relabel(Work wk, ipp_params p);
 
-__global__ void k_fill_i32(int32_t* a, int64_t n, int32_t v);
 __global__ void k_fill_i64(int64_t* a, int64_t n, int64_t v);
 __global__ void k_resolve(Work wk, ipp_params p);
 __global__ void k_heads(Work wk, ipp_params p);
