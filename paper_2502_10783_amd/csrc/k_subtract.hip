@@ -3,7 +3,7 @@
 //   K(u, v) = sum_n a_n(x, y) exp(-(u^2 + v^2) / (2 sigma_k^2)) u^i v^j
 // and the difference D = (I + B) - R (x) K is written.  As in the paper's
 // GPU design, the image is cut into stamps (21 x 21 by default); here one
-// wavefront handles one stamp: the stamp's kernel (a_n and B evaluated at
+// wavefront handles one stamp, or a workgroup a larger one: the stamp's kernel (a_n and B evaluated at
 // the stamp centre) is built in binary64 and kept in LDS as binary32, the
 // template tile with its (2 hw)-pixel margin is staged in LDS (zero outside
 // the frame), and each output pixel sums its (2hw+1)^2 products in binary32
