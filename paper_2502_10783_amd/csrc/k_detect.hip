@@ -152,12 +152,13 @@ __global__ __launch_bounds__(kBlock) void k_bkg_maps(Work wk, ipp_params p) {
 // inside a row), and counts, bounding boxes and border contact are
 // accumulated once per run.  Every pass over runs walks the dense list.
 //
-// Sixteen 4096^2 frames: 970 us (1057 us before); the pixels alone (load, spline,
-// threshold, store) take 545 us, near the copy rate.  The rest is latency: a
-// tile's labelling is a chain of barriers, which four tiles a compute unit
-// overlap only in part, so every scan is done by each wave for itself
-// (wave_inclusive_scan), 7 barriers against 11, and the node tables are
-// requested ahead of the spline weights.
+// Sixteen 4096^2 frames: 970 us (1057 us before); the pixels alone (load,
+// spline, threshold, store; a copy of the kernel cut down to them) take 545 us,
+// near the copy rate.  The rest is latency: a tile's labelling is a chain of
+// barriers, which four tiles a compute unit (all its wave slots) overlap only
+// in part, so every scan is done by each wave for itself (wave_inclusive_scan),
+// 7 barriers against 11, and the node tables are requested ahead of the spline
+// weights.
 // ---------------------------------------------------------------------
 template <int TH, int TW, bool FUSED, bool CONN8, int NT>
 __global__ __launch_bounds__(NT) void k_tile_ccl(Work wk, ipp_params p,

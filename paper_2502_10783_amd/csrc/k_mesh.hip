@@ -461,15 +461,16 @@ __global__ __launch_bounds__(kBlock) void k_mesh_stats(Work wk,
 // with wave-level histograms of 16-bit counts (two per LDS word), ballot
 // counts, and one fused pass per clipping step that counts the new set and
 // sums its moments about a fixed shift c0 (the sample median).
-// Bound by vector instructions (5000 a region of 64^2, 77 % of the time) and,
-// with few regions, by one wavefront's chain.  Per pixel: a key in two
-// instructions, its bin in three (WaveBins), the count's address and half in
-// four, and two comparisons a pass with what lies outside treated only in
-// the registers that hold any; gathered keys take their slots from ballots
-// (an LDS counter cost a round trip for every register with a key), and eight
-// registers' comparisons are made ahead of their branches.  Sixteen 4096^2
-// frames 815 -> 590 us (653 with each branch behind its comparison, 609 with four
-// regions a workgroup), one 512^2 frame 45 -> 30 us.
+// Bound by vector instructions (4,700 to 5,250 a region of 64^2; issuing them
+// takes 81 to 88 % of the time) and, with few regions, by one wavefront's
+// chain.  Per pixel: a key in two instructions, its bin in three (WaveBins),
+// the count's address and half in four, and two comparisons a pass with what
+// lies outside treated only in the registers that hold any; gathered keys take
+// their slots from ballots (an LDS counter cost a round trip for every register
+// with a key), and eight registers' comparisons are made ahead of their
+// branches.  Sixteen 4096^2 frames 815 -> 590 us (653 with each branch behind
+// its comparison, 609 with four regions a workgroup), one 512^2 frame 45 -> 30
+// us.
 namespace {
 
 constexpr int kWBins = 2048;       // level-1 bins: 32 per lane

@@ -796,11 +796,11 @@ __attribute__((amdgpu_waves_per_eu(NS <= 512 ? 4 : 1))) void k_aperture_t(
 // Centroid refinement: one wavefront per row, every step in the wave
 // (PHOT: the photometry of the first evaluation is written too; a
 // variant of its own, so that the plain refinement keeps its registers).
-// Bound by vector instructions (3300 an evaluation, radii 5/8/12) and by the
-// latency of what each waits for, so wavefronts in flight count: four a SIMD
-// (128 registers, up to 12 spilled, 152 KB of LDS a compute unit) against
-// three: 8044 against 8829 us for 1.0e5 sources, 10 steps (four rows a
-// workgroup; 6945 with one).  With the atan
+// Bound by vector instructions (2,510 an evaluation, radii 5/8/12; issuing
+// them takes 92 % of the time) and by the latency of what each waits for, so
+// wavefronts in flight count: four a SIMD (128 registers, up to 12 spilled,
+// 152 KB of LDS a compute unit) against three: 8044 against 8829 us for 1.0e5
+// sources, 10 steps (four rows a workgroup; 6945 with one).  With the atan
 // table in LDS, 32-bit task lists and three a SIMD it was 9900 us.
 template <int NS, bool PHOT>
 __global__ __launch_bounds__(kRowThreads)

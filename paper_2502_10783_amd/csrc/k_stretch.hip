@@ -202,8 +202,8 @@ __device__ __forceinline__ void asinh_bwd_one(float x, float g, double a,
 
 // HBM traffic of 12 B per element (read v and dL/dy, write dL/dv); with a
 // division, a square root and a logarithm's division per element in binary64
-// it was bound by their issue (293 us for 67.1 million elements); 70 vector
-// instructions per element now fill 124 of its 187 us (4.3 TB/s).  Loading
+// it was bound by their issue (293 us for 67.1 million elements); 67 vector
+// instructions per element now fill 114 of its 187 us (4.3 TB/s).  Loading
 // the next group before working on one changes nothing (190 us).
 __global__ __launch_bounds__(kBlock) void k_asinh_bwd(const float* v,
                                                       const float* dy,

@@ -105,11 +105,12 @@ static SubLayout sub_layout(const SubBasis& bs, int R) {
 // time in binary32, taps in order, and the columns in binary64.  The kernel
 // is built from its separable factors: 15 products per tap for the default
 // 49 terms instead of 49, and no exponential per tap.
-// Bound by VALU issue (4,700 vector instructions per stamp, 3,087 of them
-// the convolution's FMAs): 344 -> 220 us for the 10.3 Mpx of two frame pairs
-// of 2047 x 3001 and 2048 x 2048 (26 -> 41 TFLOP/s of the 78.6 that unpacked
-// FP32 FMAs reach).  Stamps up to 21 pixels take the narrow tile (7 KB: four
-// wavefronts per SIMD fit the LDS), larger ones the wide one (16 KB).
+// Bound by VALU issue (5,290 vector instructions per stamp, 3,087 of them
+// the convolution's FMAs; issuing them takes 95 % of the time): 344 -> 219 us
+// for the 10.3 Mpx of two frame pairs of 2047 x 3001 and 2048 x 2048 (26 -> 41
+// TFLOP/s of the 78.6 that unpacked FP32 FMAs reach).  Stamps up to 21 pixels
+// take the narrow tile (7 KB: four wavefronts per SIMD fit the LDS), larger
+// ones the wide one (16 KB).
 // SHARED: a workgroup of one wavefront per 64 threads' outputs takes a stamp
 // (see launch_subtract), each step split over its threads; the sums are the
 // same.
