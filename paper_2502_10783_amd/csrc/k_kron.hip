@@ -602,9 +602,11 @@ __attribute__((amdgpu_waves_per_eu(3))) void k_kron(Work wk, ipp_sources src,
 // summing the parts in turn; the additions are the same.  (1000 rows of
 // windows of 4,489 and 12,100 pixels, with room and without: 193 and
 // 208 us; up to 512 rows one after the other in a workgroup: 24,970.)
-// A launch is bound by the longest part: 2048 pixels, 32 us for all parts of
-// four 4096 x 4096 frames (4096 pixels: 59 us); windows over 4096 pixels go in
-// parts, one wavefront takes about 20 us for such a window.  Finishing the
+// A launch is bound by the longest part: with 2048 pixels pass 2 of four
+// 4096 x 4096 frames takes 34 us and pass 1 21, with 4096 pixels the longer
+// took nearly twice that (59 against 32, before it finished the rows).
+// Windows over 4096 pixels go in parts; one wavefront takes about 20 us for
+// such a window.  Finishing the
 // rows in two kernels of their own cost every call two launches more (20 rows
 // of a 256 x 256 frame: 38 against 33.5 us) and read every row's windows again
 // (13 us on the four frames; 5 here).  Pass 1 takes 84 registers: at eight

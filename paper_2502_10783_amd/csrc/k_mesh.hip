@@ -462,7 +462,7 @@ __global__ __launch_bounds__(kBlock) void k_mesh_stats(Work wk,
 // counts, and one fused pass per clipping step that counts the new set and
 // sums its moments about a fixed shift c0 (the sample median).
 // Bound by vector instructions (4,700 to 5,250 a region of 64^2; issuing them
-// takes 81 to 88 % of the time) and, with few regions, by one wavefront's
+// takes 80 to 90 % of the time) and, with few regions, by one wavefront's
 // chain.  Per pixel: a key in two instructions, its bin in three (WaveBins),
 // the count's address and half in four, and two comparisons a pass with what
 // lies outside treated only in the registers that hold any; gathered keys take

@@ -797,7 +797,7 @@ __attribute__((amdgpu_waves_per_eu(NS <= 512 ? 4 : 1))) void k_aperture_t(
 // (PHOT: the photometry of the first evaluation is written too; a
 // variant of its own, so that the plain refinement keeps its registers).
 // Bound by vector instructions (2,510 an evaluation, radii 5/8/12; issuing
-// them takes 92 % of the time) and by the latency of what each waits for, so
+// them takes 90 % of the time) and by the latency of what each waits for, so
 // wavefronts in flight count: four a SIMD (128 registers, up to 12 spilled,
 // 152 KB of LDS a compute unit) against three: 8044 against 8829 us for 1.0e5
 // sources, 10 steps (four rows a workgroup; 6945 with one).  With the atan

@@ -106,7 +106,7 @@ static SubLayout sub_layout(const SubBasis& bs, int R) {
 // is built from its separable factors: 15 products per tap for the default
 // 49 terms instead of 49, and no exponential per tap.
 // Bound by VALU issue (5,290 vector instructions per stamp, 3,087 of them
-// the convolution's FMAs; issuing them takes 95 % of the time): 344 -> 219 us
+// the convolution's FMAs; issuing them takes over 90 % of the time): 344 -> 219 us
 // for the 10.3 Mpx of two frame pairs of 2047 x 3001 and 2048 x 2048 (26 -> 41
 // TFLOP/s of the 78.6 that unpacked FP32 FMAs reach).  Stamps up to 21 pixels
 // take the narrow tile (7 KB: four wavefronts per SIMD fit the LDS), larger
